@@ -142,9 +142,9 @@ struct TdLayout {
 };
 
 // The float32 fc1 weight gradient of a large batch and a 512-wide hidden
-// layer is computed as kGemmF16WgradSlices k-slices of partial sums (larger
+// layer is computed as kGemmX6WgradSlices k-slices of partial sums (larger
 // tiles), which the finalize adds.
-bool fc1w_split(const NetInfo& ni, int B) { return !ni.bf16 && B >= kGemmF16SliceMinRows && ni.H >= 512; }
+bool fc1w_split(const NetInfo& ni, int B) { return !ni.bf16 && B >= kGemmX6SliceMinRows && ni.H >= 512; }
 
 constexpr int kShareMinBatch = 101;
 
@@ -201,7 +201,7 @@ TdLayout td_layout(const NetInfo& ni, int B, void* ws) {
         for (int w = 0; w < 2; ++w) t.fpk[0][w] = cv.take<float>(ws, fwd_pack_floats(CONV_S2));
     }
     if (ni.bf16) t.dz1h = cv.take<__bf16>(ws, (int64_t)B * ni.H);
-    if (fc1w_split(ni, B)) t.fc1w_part = cv.take<float>(ws, (int64_t)kGemmF16WgradSlices * ni.H * ni.flat);
+    if (fc1w_split(ni, B)) t.fc1w_part = cv.take<float>(ws, (int64_t)kGemmX6WgradSlices * ni.H * ni.flat);
     t.bytes = cv.off;
     return t;
 }
@@ -487,7 +487,7 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
         // same rounding the staging would apply)
         const float* dzA = t.dz1h ? (const float*)t.dz1h : t.dz1;
         if (t.fc1w_part) {   // k-slices of ceil(B / 128) * 64 samples (the last one at most that)
-            constexpr int S = kGemmF16WgradSlices;
+            constexpr int S = kGemmX6WgradSlices;
             RUN(DQN_K_FC1_WGRAD,
                 launch_gemm(GEMM_TN, ni.H, ni.flat, B, t.dz1, ni.H, xlast, ni.flat, t.fc1w_part, ni.flat, S,
                             (B + 64 * S - 1) / (64 * S) * 64, (int64_t)ni.H * ni.flat, nullptr, false, st));
@@ -581,7 +581,7 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
     fa.fc1w_off = ni.w_off[L];
     fa.fc1w_count = (int64_t)ni.H * ni.flat;
     fa.fc1w_part = t.fc1w_part;
-    fa.fc1w_slices = t.fc1w_part ? kGemmF16WgradSlices : 0;
+    fa.fc1w_slices = t.fc1w_part ? kGemmX6WgradSlices : 0;
     fa.spart = t.spart;
     fa.schunks = finalize_sample_chunks(B);
     if (upd)
