@@ -369,7 +369,7 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
 
     // The large network's conv2 and conv3 kernels that hold their weights in
     // registers load them from copies in per-lane order, written beside the
-    // first layer (launch_conv1_u8_fwd): the fp32 forward's two scaled float16 planes of both weight
+    // first layer (launch_conv1_u8_fwd): the fp32 forward's three bfloat16 planes of both weight
     // sets, and the input gradients' weights of both precisions (instead of
     // gathering 64 to 144 scattered words per lane; the gather dominated a
     // workgroup's first sample: batch 256, conv2's fp32 input gradient 33 ->

@@ -92,6 +92,21 @@ def test_td_gradient_under_unit_rescaling(dev, name, B, layer):
     assert_grad_close(shape, g * f, ref["grad"], TOL)
 
 
+# The conv kernels: large to 64 states (a workgroup per tile) and above (runs
+# of samples, the last short at 301), small from 150.
+@pytest.mark.parametrize("name,layer,B", [("large", layer, B) for layer in ("conv1", "conv2", "conv3") for B in (20, 65, 301)] +
+                         [("small", layer, B) for layer in ("conv1", "conv2") for B in (150, 600)])
+def test_forward_under_unit_rescaling(dev, name, layer, B):
+    net, shape = NETS[name]
+    th = di.xavier_theta(shape, 800 + B, bias_scale=0.05)
+    f = _rescaling(shape, layer, 1 + B)
+    s = di.random_states(B, 801 + B)
+    say(f"[magnitudes] forward net={name} batch={B} rescaled units of {layer}")
+    q = _forward(dev, net, (th * f).astype(F32), s)
+    rows = np.unique(np.linspace(0, B - 1, 30).astype(int))
+    assert_close(q[rows], oracle.forward_q(shape, th, s[rows]), TOL, "q")
+
+
 @pytest.mark.parametrize("name,B", [("large", 150), ("large", 1100), ("small", 300)])
 def test_forward_of_quiet_states_among_ordinary_ones(dev, name, B):
     net, shape = NETS[name]
