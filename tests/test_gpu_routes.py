@@ -15,16 +15,17 @@ pytestmark = pytest.mark.gpu
 F32 = np.float32
 
 
-# 32 | 33: the split conv forward (64 samples of s and s'); 63 | 64 and
-# 127 | 128: the fc1 forward and its gradients on f16 MFMA (small network: 127
-# | 128 and 255 | 256); 128 | 129: the eight-lane finalize; small network, 80 |
-# 81: the fused and the sample-walking conv kernels; 85 | 86 and 128 | 129: a
-# sample or a run of them per workgroup of the two backward passes (301: runs
-# with a remainder).
+# 31 | 32: the fc1 forward on bf16 MFMA (64 rows of s and s'; small network 63 |
+# 64); 32 | 33: a workgroup per conv output tile (64 samples of s and s');
+# 127 | 128: the fc1 gradients on bf16 MFMA (small network 255 | 256); 128 |
+# 129: the eight-lane finalize; small network, 80 | 81: the fused and the
+# sample-walking conv kernels; 85 | 86 and 128 | 129: a sample or a run of them
+# per workgroup of the two backward passes (301: runs with a remainder).
 @pytest.mark.parametrize("name,B,target", [
-    ("large", 1, "held"), ("large", 24, "held"), ("large", 32, "held"), ("large", 33, "same"), ("large", 63, "held"),
-    ("large", 85, "held"), ("large", 86, "same"), ("large", 127, "same"), ("large", 128, "same"), ("large", 129, "held"),
-    ("large", 301, "held"), ("small", 80, "same"), ("small", 81, "held"), ("small", 127, "held"),
+    ("large", 1, "held"), ("large", 24, "held"), ("large", 31, "held"), ("large", 32, "held"), ("large", 33, "same"),
+    ("large", 63, "held"), ("large", 85, "held"), ("large", 86, "same"), ("large", 127, "same"), ("large", 128, "same"),
+    ("large", 129, "held"), ("large", 301, "held"), ("small", 63, "held"), ("small", 64, "same"),
+    ("small", 80, "same"), ("small", 81, "held"), ("small", 127, "held"),
     ("small", 128, "same"), ("small", 129, "held"), ("small", 255, "same"), ("small", 256, "held")])
 def test_td_gradient_at_route_edges(dev, name, B, target):
     net, shape = NETS[name]
@@ -61,7 +62,7 @@ def test_bf16_td_gradient_at_route_edges(dev, B):
     assert max(errs.values()) <= BF16_TOL, errs
 
 
-@pytest.mark.parametrize("net,B", [(dq.NET_SMALL, 149), (dq.NET_SMALL, 150), (dq.NET_LARGE, 1), (dq.NET_LARGE, 64),
+@pytest.mark.parametrize("net,B", [(dq.NET_SMALL, 149), (dq.NET_SMALL, 150), (dq.NET_LARGE, 1), (dq.NET_LARGE, 63), (dq.NET_LARGE, 64),
                                    (dq.NET_LARGE, 65), (dq.NET_LARGE_BF16, 1), (dq.NET_LARGE_BF16, 67)])
 def test_forward_at_route_edges(dev, net, B):
     import torch
