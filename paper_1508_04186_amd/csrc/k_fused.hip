@@ -699,7 +699,7 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
     if ((int)blockIdx.x >= p.blocks) {   // uniform
         const int q = (int)blockIdx.x - p.blocks, half = threadIdx.x >> 8;
         weight_repack_job<COUT == 16>(p.rp, (int)(p.jobs >> (4 * (q / U8F_RBLOCKS))) & 15, 2 * (q % U8F_RBLOCKS) + half,
-                                      threadIdx.x & 255, (uint32_t*)smem + 4 * half);
+                                      threadIdx.x & 255);
         return;
     }
     using E = std::conditional_t<PARTS == 2, _Float16, __bf16>;

@@ -92,6 +92,24 @@ def test_td_gradient_under_unit_rescaling(dev, name, B, layer):
     assert_grad_close(shape, g * f, ref["grad"], TOL)
 
 
+# The input gradients: what reaches the layers below the rescaled one, as the
+# gradient of their weights.  A sample a workgroup, and runs of them (301).
+@pytest.mark.parametrize("name,layer,B", [("large", "conv3", 40), ("large", "conv3", 301), ("large", "conv2", 40),
+                                          ("large", "conv2", 301), ("small", "conv2", 90), ("small", "conv2", 300)])
+def test_input_gradients_under_unit_rescaling(dev, name, layer, B):
+    net, shape = NETS[name]
+    th = di.xavier_theta(shape, 900 + B, bias_scale=0.05)
+    f = _rescaling(shape, layer, 2 + B)
+    s, sn, a, r, t = _td_inputs(shape, B, 901 + B, theta=th)
+    say(f"[magnitudes] input gradients net={name} batch={B} rescaled units of {layer}")
+    g, _, _, _ = _run_td(dev, net, (th * f).astype(F32), None, s, sn, a, r, t, 0.99)
+    ref = oracle.td_gradient(shape, th, None, s, sn, a, r, t, float(F32(0.99)))["grad"]
+    for below in ("conv1.W", "conv1.b", "conv2.W", "conv2.b"):
+        if below[:5] < layer:
+            sl, _ = _span(shape, below)
+            assert_close(g[sl], ref[sl], TOL, below)
+
+
 # The conv kernels: large to 64 states (a workgroup per tile) and above (runs
 # of samples, the last short at 301), small from 150.
 @pytest.mark.parametrize("name,layer,B", [("large", layer, B) for layer in ("conv1", "conv2", "conv3") for B in (20, 65, 301)] +
