@@ -538,7 +538,7 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
         }
         if (!ni.bf16) {
             RUN(DQN_K_CONV2_BWD + (l - 1),
-                launch_conv_bwd_f16(ni.conv[l], t.act[l - 1], t.dconv[l], B, t.wpart[l], t.bpart[l], t.dconv[l - 1],
+                launch_conv_bwd_x6(ni.conv[l], t.act[l - 1], t.dconv[l], B, t.wpart[l], t.bpart[l], t.dconv[l - 1],
                                     l == 1 ? t.wpk2 : t.wpk3, st));
             continue;
         }

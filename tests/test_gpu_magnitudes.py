@@ -14,7 +14,7 @@ import pytest
 import dqn_inputs as di
 import oracle
 import paper_1508_04186_amd as dq
-from gpu_util import assert_close, assert_grad_close, dev_tensor, host, say
+from gpu_util import MARGIN_MIN, assert_close, assert_grad_close, dev_tensor, host, say
 from test_gpu_parity import NETS, _run_td, _td_inputs
 
 pytestmark = pytest.mark.gpu
@@ -24,6 +24,8 @@ F32 = np.float32
 # 2^-24 each, random in sign, on sums that cancel to about a tenth of their
 # terms.  (A value kept to 2^-40 of a neighbour 2^30 larger is off by 1e-3.)
 TOL = 1e-5
+QUIET_TENSORS = {"small": ["conv2.W", "conv2.b", "fc1.W", "fc1.b"],
+                 "large": ["conv2.W", "conv2.b", "conv3.W", "conv3.b", "fc1.W", "fc1.b"]}
 
 
 def _span(shape, name):
@@ -74,8 +76,8 @@ def _forward(dev, net, th, s):
 
 # Sizes of the fc1 kernels: split forward and gradients (large from 64 states
 # of a step, 128 of a forward; small 128 and 256), 1,024: 128-wide tiles.
-@pytest.mark.parametrize("name,B", [("large", 40), ("large", 130), ("small", 90), ("small", 257)])
-@pytest.mark.parametrize("layer", ["fc1"])
+@pytest.mark.parametrize("name,B,layer", [("large", B, layer) for layer in ("fc1", "conv3", "conv2") for B in (40, 130, 301)] +
+                         [("small", B, layer) for layer in ("fc1", "conv2") for B in (90, 257)])
 def test_td_gradient_under_unit_rescaling(dev, name, B, layer):
     net, shape = NETS[name]
     th = di.xavier_theta(shape, 500 + B, bias_scale=0.05)
@@ -108,6 +110,63 @@ def test_input_gradients_under_unit_rescaling(dev, name, layer, B):
         if below[:5] < layer:
             sl, _ = _span(shape, below)
             assert_close(g[sl], ref[sl], TOL, below)
+
+
+def _two_networks(shape, seed):
+    """Parameters of two networks side by side, their first halves of the
+    channels seeing the oldest frame only and their second halves the newest
+    only, with negative biases (a half that sees black is silent); the output
+    rows of the lower actions are 2^-16 of the others.  Returns them and the
+    mask of the first network's parameters."""
+    th = di.xavier_theta(shape, seed)
+    mine = np.zeros(th.size, bool)
+    rng = np.random.default_rng(seed + 1)
+    names = [f"conv{i + 1}" for i in range(len(shape.conv))] + ["fc1"]
+    for name in names:
+        sl, shp = _span(shape, name + ".W")
+        w, m = th[sl].reshape(shp), mine[sl].reshape(shp)
+        ho, hi = shp[0] // 2, shp[1] // 2
+        if name == "conv1":
+            w[:, 1:3] = 0
+            hi = 1
+        w[:ho, hi:] = 0
+        w[ho:, :(3 if name == "conv1" else hi)] = 0
+        m[:ho, :hi] = True
+        sl, _ = _span(shape, name + ".b")
+        th[sl] = rng.uniform(-0.01, -0.001, shp[0]).astype(F32)
+        mine[sl][:ho] = True
+    sl, shp = _span(shape, "fc2.W")
+    th[sl].reshape(shp)[:shp[0] // 2] *= F32(2.0) ** -16
+    return th, mine
+
+
+# Slots and tiles that hold samples of both kinds: half of the samples show
+# only the oldest frame and have TD errors and output weights of 2^-16 of the
+# others', so the first network's gradient is theirs alone, 2^-32 beside the
+# second's.
+@pytest.mark.parametrize("name,B", [("large", 301), ("large", 600), ("small", 300)])
+def test_gradient_of_quiet_samples_among_ordinary_ones(dev, name, B):
+    net, shape = NETS[name]
+    th, mine = _two_networks(shape, 1000 + B)
+    cand = di.random_states(2 * B, 1001 + B)
+    quiet = np.arange(2 * B) % 2 == 1
+    cand[quiet, 1:] = 0
+    cand[~quiet, :3] = 0
+    keep = np.nonzero(oracle.relu_margins(shape, th, cand) >= MARGIN_MIN)[0][:B]
+    assert keep.size == B
+    s, quiet = cand[keep], quiet[keep]
+    a, r, t = di.random_transitions(B, shape.n_actions // 2, 1002 + B)
+    a[~quiet] += shape.n_actions // 2
+    r = (r + F32(0.5)) * np.where(quiet, F32(2.0) ** -16, F32(1.0))
+    t[quiet] = 1
+    sn = di.random_states(B, 1003 + B)
+    say(f"[magnitudes] gradient net={name} batch={B} quiet samples")
+    g, _, _, _ = _run_td(dev, net, th, None, s, sn, a, r.astype(F32), t, 0.99)
+    ref = oracle.td_gradient(shape, th, None, s, sn, a, r.astype(F32), t, float(F32(0.99)))["grad"]
+    for part in QUIET_TENSORS[name]:
+        sl, _ = _span(shape, part)
+        assert_close(g[sl][mine[sl]], ref[sl][mine[sl]], TOL, part)
+        assert_close(g[sl][~mine[sl]], ref[sl][~mine[sl]], TOL, part + " of the others")
 
 
 # The conv kernels: large to 64 states (a workgroup per tile) and above (runs
