@@ -59,11 +59,12 @@ typedef enum {
 /* Arithmetic of the layer contractions (dqn_net.precision):
  *   DQN_FP32  float32 operands and accumulation.  Some contractions run on
  *             16-bit matrix instructions with each float32 operand split into
- *             terms whose products accumulate in float32: three exact
- *             bfloat16 terms, or two float16 terms of the operand scaled by a
- *             power of two (per sample, channel or tile, from the largest
- *             magnitude in it); input bytes are exact in either.  Their error
- *             against float64 is that of float32 sums;
+ *             three bfloat16 terms whose products accumulate in float32.  The
+ *             terms hold all 24 bits of the operand (from magnitudes of
+ *             2^-110 on) and have its exponent, so the error against float64
+ *             is that of float32 sums whatever magnitudes stand side by side,
+ *             and a state or sample that overflows spoils no other one's
+ *             results (input bytes are exact in one term);
  *   DQN_BF16  the bf16-input variant, large network only: every operand of
  *             the conv and fc1 contractions (weights, input activations,
  *             back-propagated gradients) is rounded to bfloat16 (round to

@@ -647,11 +647,11 @@ hipError_t launch_conv_s12_bwd(const ConvIn& in, const float* act1, const float*
 
 // ---------------------------------------------------------------------------
 // conv1 forward on byte input (4 channels 84x84, 8x8 stride 4 -> 20x20) for
-// many samples: a workgroup splits its weights, scaled per output channel, into
-// two float16 planes once (split2; PARTS = 2), or rounds them to one bf16 plane
+// many samples: a workgroup splits its weights into three bf16 planes once
+// (exact, as above; PARTS = 3), or rounds them to one bf16 plane
 // (the bf16-input variant; PARTS = 1), then walks its samples with the next
 // sample's bytes loaded into registers while the current one is computed.
-// Each sample is staged in LDS already converted to 16 bits (exact for
+// Each sample is staged in LDS already converted to bfloat16 (exact for
 // bytes), once per byte, so an A operand (eight consecutive bytes of one
 // input row) is two 8-byte LDS reads; converting in the MFMA loop had
 // converted every byte four times (the 8x8 windows at stride 4 overlap) and
@@ -681,7 +681,7 @@ struct U8FwdParams {
 constexpr int U8F_RBLOCKS = kRepackChannels / 2;
 
 constexpr size_t u8f_lds(int cout, int parts) {
-    return (size_t)C0 * H0 * H0 * 2 + (size_t)parts * cout * RS1 * 2 + (size_t)cout * 8;
+    return (size_t)C0 * H0 * H0 * 2 + (size_t)parts * cout * RS1 * 2 + (size_t)cout * 4;
 }
 
 template <int COUT, int PARTS>
@@ -702,14 +702,10 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
                                       threadIdx.x & 255);
         return;
     }
-    using E = std::conditional_t<PARTS == 2, _Float16, __bf16>;
-    using E8 = std::conditional_t<PARTS == 2, f16x8, bf16x8>;
-    using E4 = std::conditional_t<PARTS == 2, f16x4, bf16x4>;
-    E* s_in = (E*)smem;                          // [REC]
-    E* s_w = s_in + REC;                         // [PARTS][COUT][RS1]
-    float* s_b = (float*)(s_w + PARTS * PL);     // bias [COUT], factors of the sums [COUT]
-    float* s_f = s_b + COUT;
-    static_assert(PARTS == 1 || PARTS == 2, "two-term split or bf16 rounding");
+    __bf16* s_in = (__bf16*)smem;                // [REC]
+    __bf16* s_w = s_in + REC;                    // [PARTS][COUT][RS1]
+    float* s_b = (float*)(s_w + PARTS * PL);
+    static_assert(PARTS == 1 || PARTS == 3, "exact split or bf16 rounding");
 
     const bool second = (int)blockIdx.x >= p.blocks_a;
     const int blk = second ? (int)blockIdx.x - p.blocks_a : (int)blockIdx.x;
@@ -742,8 +738,7 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
             if (e < RV) vin[u] = src[e];
         }
     };
-    // sixteen bytes -> sixteen float16 (bytes under an exponent of 1024, which
-    // is then subtracted) or bf16 (the upper halves of the exact floats)
+    // sixteen bytes -> sixteen bf16 (the upper halves of the exact floats)
     auto store_in = [&]() {
 #pragma unroll
         for (int u = 0; u < RPER; ++u) {
@@ -753,15 +748,6 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
                 uint32_t h[8];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    if constexpr (PARTS == 2) {
-                        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-                        const f16x2 k = {(_Float16)1024.f, (_Float16)1024.f};
-                        const uint32_t a = __builtin_amdgcn_perm(0x64646464u, w[q], 0x04010400u);
-                        const uint32_t b = __builtin_amdgcn_perm(0x64646464u, w[q], 0x04030402u);
-                        h[2 * q] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, a) - k);
-                        h[2 * q + 1] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, b) - k);
-                        continue;
-                    }
                     const uint32_t f0 = __builtin_bit_cast(uint32_t, (float)(w[q] & 0xffu));
                     const uint32_t f1 = __builtin_bit_cast(uint32_t, (float)((w[q] >> 8) & 0xffu));
                     const uint32_t f2 = __builtin_bit_cast(uint32_t, (float)((w[q] >> 16) & 0xffu));
@@ -776,38 +762,23 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
         }
     };
 
-    // weights -> PARTS planes [part][o][k], a wave per output channel and pass
-    // (its scale from the wave's largest magnitude); bias
+    // weights -> PARTS bf16 planes [part][o][k] (exact split, or rounding); bias
     load_in(j0);
-    static_assert(KW1 / 4 == 64 && COUT % (U8F_WG / 64) == 0, "a wave per channel");
     constexpr float inv255 = (float)(1.0 / 255.0);
-#pragma unroll
-    for (int u = 0; u < COUT / (U8F_WG / 64); ++u) {
-        const int e = t + u * U8F_WG, o = e / 64, k = 4 * (e % 64);
+    for (int e = t; e < COUT * KW1 / 4; e += U8F_WG) {
         const f4 w = ((const f4*)W)[e];
-        if constexpr (PARTS == 2) {
-            uint32_t m = 0;
+        const int o = (4 * e) / KW1, k = (4 * e) % KW1;
+        bf16x4 v[3];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) m = max(m, abs_bits(w[i]));
-            const Pow2 sc = f16_scale(wave_max(m));
-            E4 hv, lv;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                E hi, lo;
-                split2(w[i], sc.scale, hi, lo);
-                hv[i] = hi;
-                lv[i] = lo;
-            }
-            *(E4*)(s_w + o * RS1 + k) = hv;
-            *(E4*)(s_w + PL + o * RS1 + k) = lv;
-            if (k == 0) s_f[o] = sc.inv;
-        } else {
-            E4 hv;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) hv[i] = (E)w[i];
-            *(E4*)(s_w + o * RS1 + k) = hv;
-            if (k == 0) s_f[o] = 1.f;
+        for (int i = 0; i < 4; ++i) {
+            __bf16 hi, mid, lo;
+            split3(w[i], hi, mid, lo);
+            v[0][i] = hi;
+            v[1][i] = mid;
+            v[2][i] = lo;
         }
+#pragma unroll
+        for (int part = 0; part < PARTS; ++part) *(bf16x4*)(s_w + part * PL + o * RS1 + k) = v[part];
     }
     if (t < COUT) s_b[t] = bias[t];
     side.fetch(p.side, side_on, t);   // in flight during the first sample
@@ -828,9 +799,10 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
         store_in();
         __syncthreads();
         if (j + 1 < j1) load_in(j + 1);          // in flight during this sample
-        f4 acc[PARTS][MPW][NT];   // sums per weight plane
+        constexpr int SUMS = PARTS == 3 ? 2 : 1;
+        f4 acc[SUMS][MPW][NT];   // sums of the weights' first plane, and of the two smaller ones
 #pragma unroll
-        for (int part = 0; part < PARTS; ++part)
+        for (int part = 0; part < SUMS; ++part)
 #pragma unroll
             for (int i = 0; i < MPW; ++i)
 #pragma unroll
@@ -838,25 +810,25 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
 #pragma unroll
         for (int kb = 0; kb < KW1 / 32; ++kb) {
             const int c = kb >> 1, ky = (kb & 1) * 4 + g;
-            E8 b[NT][PARTS];
+            bf16x8 b[NT][PARTS];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int part = 0; part < PARTS; ++part)
-                    b[nt][part] = *(const E8*)(s_w + part * PL + (nt * 16 + li) * RS1 + kb * 32 + 8 * g);
+                    b[nt][part] = *(const bf16x8*)(s_w + part * PL + (nt * 16 + li) * RS1 + kb * 32 + 8 * g);
 #pragma unroll
             for (int i = 0; i < MPW; ++i) {
                 if (i < ntile) {
                     // bytes (c, 4 ra + ky, 4 xa .. 4 xa + 7): two 8-byte reads
-                    const E* ap = s_in + (c * H0 + ky) * H0 + abase[i];
+                    const __bf16* ap = s_in + (c * H0 + ky) * H0 + abase[i];
                     const uint2 lo = *(const uint2*)ap, hi = *(const uint2*)(ap + 4);
-                    const E8 a = __builtin_bit_cast(E8, uint4{lo.x, lo.y, hi.x, hi.y});
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, uint4{lo.x, lo.y, hi.x, hi.y});
 #pragma unroll
                     for (int part = PARTS - 1; part >= 0; --part)
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
-                            if constexpr (PARTS == 2) acc[part][i][nt] = mfma16x16x32f16(a, b[nt][part], acc[part][i][nt]);
-                            else acc[part][i][nt] = mfma16x16x32bf16(a, b[nt][part], acc[part][i][nt]);
+                            f4& c = acc[part ? 1 : 0][i][nt];
+                            c = mfma16x16x32bf16(a, b[nt][part], c);
                         }
                 }
             }
@@ -870,13 +842,13 @@ __global__ __launch_bounds__(U8F_WG) void conv1_u8_fwd_kernel(U8FwdParams p) {
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     const int o = nt * 16 + li;
-                    const float bo = s_b[o], f = s_f[o];
+                    const float bo = s_b[o];
                     f4 v;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         float x = acc[0][i][nt][r];
-                        if constexpr (PARTS == 2) x += acc[1][i][nt][r];
-                        v[r] = fmaxf(x * f * inv255 + bo, 0.f);
+                        if constexpr (PARTS == 3) x += acc[1][i][nt][r];
+                        v[r] = fmaxf(x * inv255 + bo, 0.f);
                     }
                     if constexpr (PARTS == 1) {   // the bf16-input variant stores bfloat16
                         bf16x4 h;
@@ -929,9 +901,9 @@ hipError_t launch_conv1_u8_fwd(ConvId id, const ConvIn& in_a, const ConvIn& in_b
         hipLaunchKernelGGL(kern, grid, dim3(U8F_WG), lds, st, prm);
         return hipGetLastError();
     };
-    if (id == CONV_S1 && !bf16) return go(conv1_u8_fwd_kernel<16, 2>, 16, 2);
+    if (id == CONV_S1 && !bf16) return go(conv1_u8_fwd_kernel<16, 3>, 16, 3);
     if (id != CONV_L1) return hipErrorInvalidValue;
-    return bf16 ? go(conv1_u8_fwd_kernel<32, 1>, 32, 1) : go(conv1_u8_fwd_kernel<32, 2>, 32, 2);
+    return bf16 ? go(conv1_u8_fwd_kernel<32, 1>, 32, 1) : go(conv1_u8_fwd_kernel<32, 3>, 32, 3);
 }
 
 }  // namespace dqn
@@ -942,22 +914,23 @@ hipError_t launch_conv1_u8_fwd(ConvId id, const ConvIn& in_a, const ConvIn& in_b
 //                      dz[o][y][x] * byte[c][4y + ky][4x + kx],  db[o] = sum dz.
 // One workgroup of eight waves per compute unit owns all COUT x 256 outputs
 // for a run of samples (one partial-sum slot).  The contraction over pixels
-// runs on 16-bit MFMA: the bytes are exact, and dz, scaled by a power of two,
-// is split into two float16 planes (split2; PARTS = 2), two products per step;
-// the bf16-input variant takes dz rounded to one bf16 plane (PARTS = 1).  One
-// scale serves all of a workgroup's samples: it follows the largest magnitude
-// seen so far, and where a sample raises it the accumulators are rescaled
-// (exactly).  Per sample, dz is staged as the planes [part][o][pixel] and the
-// bytes, converted, as phases [c][row][kx][i] = byte[c][row][4i + kx] (i < 20),
-// so that four pixels (y, x..x+3) of one row are 8 contiguous bytes of a plane
-// and of a phase row.  Lane group g of k-step st takes pixels 32 st + 8 g + e
+// runs on v_mfma_f32_16x16x32_bf16: the bytes are exact in bfloat16, and dz
+// is split exactly into three bfloat16 planes (hi + mid + lo; PARTS = 3), so
+// the three products per step are those of the float32 dz (the two small ones
+// summed apart); the bf16-input variant takes dz rounded to one plane (PARTS =
+// 1).  Per sample, dz is staged as the planes [part][o][pixel] and the bytes as
+// phases [c][row][kx][i] = byte[c][row][4i + kx] (i < 20), so that four pixels
+// (y, x..x+3) of one row are 8 contiguous bytes of a plane and four entries of
+// a phase row.  Lane group g of k-step st takes pixels 32 st + 8 g + e
 // (e < 8), two groups of four within rows; pixels 400..415 of the last step
 // are zero in the planes.  Wave w owns N-tiles (weight columns) 2w, 2w+1 and
 // every M-tile (output channel block); the next sample's dz and bytes are
-// read into registers during the current sample's MFMAs.  With the phases two
-// bytes an entry (107 KB, 158 KB with both planes) a B operand is two 8-byte
-// reads.  The pixel-group offsets of a lane are formed once, and each k-step's
-// operands are read while the previous step multiplies.
+// read into registers during the current sample's MFMAs.  With one plane, or
+// the small network's 16 channels, the phases are staged already converted
+// (two bytes an entry, 105 KB), so a B operand is two 8-byte reads; beside
+// three planes of 32 channels the LDS has room for the bytes only, which are
+// converted as they are read.  The pixel-group offsets of a lane are formed
+// once, and each k-step's operands are read while the previous step multiplies.
 namespace dqn {
 namespace {
 
@@ -972,7 +945,12 @@ constexpr int UW_ITEMS = C0 * H0 * 5;           // (channel, row, 16-byte column
 constexpr int UW_IPER = (UW_ITEMS + UW_WG - 1) / UW_WG;
 static_assert(32 * UW_STEPS <= UW_LDZ && UW_P % 4 == 0 && H1 % 4 == 0, "pixel groups of four within rows");
 
-constexpr size_t uw_lds(int cout, int parts) { return (size_t)parts * cout * UW_LDZ * 2 + (size_t)UW_PH * 2 + 32; }
+// bytes per phase entry: two (bfloat16) where they fit beside the planes, else one
+constexpr int uw_phase_bytes(int cout, int parts) { return parts == 1 || cout == 16 ? 2 : 1; }
+constexpr size_t uw_lds(int cout, int parts) {
+    return (size_t)parts * cout * UW_LDZ * 2 + (size_t)UW_PH * uw_phase_bytes(cout, parts);
+}
+static_assert(uw_lds(16, 3) <= 160 * 1024 && uw_lds(32, 3) <= 160 * 1024 && uw_lds(32, 1) <= 160 * 1024, "fits in LDS");
 
 struct U8WgradParams {
     ConvIn in;            // network input (bytes)
@@ -990,17 +968,13 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
     constexpr int MT = COUT / 16;
     constexpr int RPW = COUT / 8;                      // dz rows staged per wave
     constexpr int CPR = UW_P / 4;                      // four-value chunks per dz row (100)
-    static_assert(PARTS == 1 || PARTS == 2, "two-term split or bf16 rounding");
-    using E = std::conditional_t<PARTS == 2, _Float16, __bf16>;
-    using E8 = std::conditional_t<PARTS == 2, f16x8, bf16x8>;
-    using E4 = std::conditional_t<PARTS == 2, f16x4, bf16x4>;
+    static_assert(PARTS == 1 || PARTS == 3, "exact split or bf16 rounding");
     constexpr bool DZ16 = PARTS == 1;
     static_assert(KW1 == 16 * 16 && COUT % 16 == 0, "16 N-tiles of weight columns, 2 per wave");
-    constexpr int PHB = 2;                 // bytes per phase entry
+    constexpr int PHB = uw_phase_bytes(COUT, PARTS);
     extern __shared__ __align__(16) unsigned char smem[];
-    E* s_dz = (E*)smem;                                             // [PARTS][COUT][UW_LDZ]
-    unsigned char* s_ph = smem + (size_t)PARTS * COUT * UW_LDZ * 2;  // [C0][H0][8][20] two-byte values
-    uint32_t* s_max = (uint32_t*)(s_ph + 2 * UW_PH);                 // [8] (PARTS = 2)
+    __bf16* s_dz = (__bf16*)smem;                                   // [PARTS][COUT][UW_LDZ]
+    unsigned char* s_ph = smem + (size_t)PARTS * COUT * UW_LDZ * 2;  // [C0][H0][8][20]
 
     const int j0 = blockIdx.x * p.spb, j1 = min(p.n, j0 + p.spb);
     if (j0 >= j1) return;  // whole workgroup
@@ -1010,7 +984,7 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
     // pixels 400 .. UW_LDZ-1 of every plane row stay zero
     for (int e = t; e < PARTS * COUT * (UW_LDZ - UW_P); e += UW_WG) {
         const int row = e / (UW_LDZ - UW_P), q = e - row * (UW_LDZ - UW_P);
-        s_dz[row * UW_LDZ + UW_P + q] = (E)0.f;
+        s_dz[row * UW_LDZ + UW_P + q] = (__bf16)0.f;
     }
 
     // next sample in registers: dz rows wave*RPW .. +RPW-1 (chunks lane, lane + 64),
@@ -1046,20 +1020,7 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
     // bias sum of row wave * RPW + halving_index<RPW>(lane) (where that is >= 0):
     // the RPW rows' wave sums by halving, in each value's wave_sum order
     float bs = 0.f;
-    auto put_max = [&]() {   // the wave's largest dz magnitude of the values in flight
-        if constexpr (!DZ16) {
-            uint32_t m = 0;
-#pragma unroll
-            for (int q = 0; q < RPW; ++q)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) m = max(m, lane + 64 * h < CPR ? abs_bits(vdz[q][h][i]) : 0u);
-            m = wave_max(m);
-            if (lane == 0) s_max[wave] = m;
-        }
-    };
-    auto stage = [&](float scale) {
+    auto stage = [&]() {
         float parts[RPW];
 #pragma unroll
         for (int q = 0; q < RPW; ++q) {
@@ -1075,16 +1036,17 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
                 } else if (ch < CPR) {
                     const f4 v = vdz[q][h];
                     part += (v[0] + v[1]) + (v[2] + v[3]);
-                    E4 hv, lv;
+                    bf16x4 pl[3];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        E hi, lo;
-                        split2(v[i], scale, hi, lo);
-                        hv[i] = hi;
-                        lv[i] = lo;
+                        __bf16 hi, mid, lo;
+                        split3(v[i], hi, mid, lo);
+                        pl[0][i] = hi;
+                        pl[1][i] = mid;
+                        pl[2][i] = lo;
                     }
-                    *(E4*)(s_dz + o * UW_LDZ + 4 * ch) = hv;
-                    *(E4*)(s_dz + (COUT + o) * UW_LDZ + 4 * ch) = lv;
+#pragma unroll
+                    for (int q3 = 0; q3 < 3; ++q3) *(bf16x4*)(s_dz + (q3 * COUT + o) * UW_LDZ + 4 * ch) = pl[q3];
                 }
             }
         }
@@ -1102,16 +1064,14 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
                     const uint32_t lo2 = __builtin_amdgcn_perm(vb[u][d + 1], vb[u][d], sel);
                     const uint32_t hi2 = __builtin_amdgcn_perm(vb[u][d + 3], vb[u][d + 2], sel);
                     const uint32_t w = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
-                    E4 h;   // the four bytes (exact)
-                    if constexpr (PARTS == 2) {   // (under an exponent of 1024, which is subtracted)
-                        const f16x4 k = {(_Float16)1024.f, (_Float16)1024.f, (_Float16)1024.f, (_Float16)1024.f};
-                        h = __builtin_bit_cast(f16x4, uint2{__builtin_amdgcn_perm(0x64646464u, w, 0x04010400u),
-                                                            __builtin_amdgcn_perm(0x64646464u, w, 0x04030402u)}) - k;
-                    } else {
+                    if constexpr (PHB == 2) {   // the four bytes as bfloat16 (exact)
+                        bf16x4 h;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) h[e] = (E)(float)((w >> (8 * e)) & 0xffu);
+                        for (int e = 0; e < 4; ++e) h[e] = (__bf16)(float)((w >> (8 * e)) & 0xffu);
+                        *(bf16x4*)(s_ph + ((row * 8 + kx) * H1 + 4 * qb) * 2) = h;
+                    } else {
+                        *(uint32_t*)(s_ph + (row * 8 + kx) * H1 + 4 * qb) = w;
                     }
-                    *(E4*)(s_ph + ((row * 8 + kx) * H1 + 4 * qb) * 2) = h;
                 }
             }
         }
@@ -1136,51 +1096,42 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
             const int y = pp < UW_P ? pp / H1 : 0, x = pp < UW_P ? pp - (pp / H1) * H1 : 0;
             po[st][h] = (S1 * y * 8 * H1 + x) * PHB;
         }
-    f4 acc[MT][2];
+    f4 acc[MT][2], low[MT][2];   // sums of dz's first plane, and of the two smaller ones
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int n = 0; n < 2; ++n) acc[m][n] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int n = 0; n < 2; ++n) acc[m][n] = low[m][n] = f4{0.f, 0.f, 0.f, 0.f};
 
     // operands of k-step st into buffer slot
-    E8 bb[2][2], aa[2][MT][PARTS];
+    bf16x8 bb[2][2], aa[2][MT][PARTS];
     auto operands = [&](int st, int slot) {
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-            const uint2 w0 = *(const uint2*)(s_ph + cb[n] + po[st][0]);
-            const uint2 w1 = *(const uint2*)(s_ph + cb[n] + po[st][1]);
-            bb[slot][n] = __builtin_bit_cast(E8, uint4{w0.x, w0.y, w1.x, w1.y});
+            if constexpr (PHB == 2) {
+                const uint2 w0 = *(const uint2*)(s_ph + cb[n] + po[st][0]);
+                const uint2 w1 = *(const uint2*)(s_ph + cb[n] + po[st][1]);
+                bb[slot][n] = __builtin_bit_cast(bf16x8, uint4{w0.x, w0.y, w1.x, w1.y});
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t w = *(const uint32_t*)(s_ph + cb[n] + po[st][h]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bb[slot][n][4 * h + e] = (__bf16)(float)((w >> (8 * e)) & 0xffu);
+                }
+            }
         }
         const int p0 = 32 * st + 8 * g;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int part = 0; part < PARTS; ++part)
-                aa[slot][m][part] = *(const E8*)(s_dz + (part * COUT + m * 16 + li) * UW_LDZ + p0);
+                aa[slot][m][part] = *(const bf16x8*)(s_dz + (part * COUT + m * 16 + li) * UW_LDZ + p0);
     };
 
     load(j0);
-    put_max();
-    uint32_t big = 0;   // largest magnitude so far: the scale in use
-    Pow2 sc{1.f, 1.f};
     for (int j = j0; j < j1; ++j) {
-        __syncthreads();  // the previous sample's reads are done; the magnitudes are written
-        if constexpr (!DZ16) {
-#pragma unroll
-            for (int w = 0; w < UW_WG / 64; ++w) big = max(big, s_max[w]);
-            const Pow2 ns = f16_scale(big);
-            if (j > j0 && ns.scale != sc.scale) {   // uniform
-                const float ratio = sc.inv * ns.scale;
-#pragma unroll
-                for (int m = 0; m < MT; ++m)
-#pragma unroll
-                    for (int n = 0; n < 2; ++n)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[m][n][r] *= ratio;
-            }
-            sc = ns;
-        }
-        stage(sc.scale);
+        __syncthreads();  // the previous sample's reads are done
+        stage();
         __syncthreads();
         if (j + 1 < j1) load(j + 1);
         operands(0, 0);
@@ -1194,11 +1145,10 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
                 for (int part = PARTS - 1; part >= 0; --part)
 #pragma unroll
                     for (int n = 0; n < 2; ++n) {
-                        if constexpr (PARTS == 2) acc[m][n] = mfma16x16x32f16(aa[sl][m][part], bb[sl][n], acc[m][n]);
-                        else acc[m][n] = mfma16x16x32bf16(aa[sl][m][part], bb[sl][n], acc[m][n]);
+                        f4& c = part ? low[m][n] : acc[m][n];
+                        c = mfma16x16x32bf16(aa[sl][m][part], bb[sl][n], c);
                     }
         }
-        if (j + 1 < j1) put_max();
     }
     // D[4g + r][li] of tile (m, n): channel m*16 + 4g + r, column (2 wave + n)*16 + li
     float* wp = p.wpart + (size_t)blockIdx.x * COUT * KW1;
@@ -1208,7 +1158,7 @@ __global__ __launch_bounds__(UW_WG) void conv1_u8_wgrad_kernel(U8WgradParams p) 
         for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                wp[(size_t)(m * 16 + 4 * g + r) * KW1 + (2 * wave + n) * 16 + li] = acc[m][n][r] * sc.inv * p.in_scale;
+                wp[(size_t)(m * 16 + 4 * g + r) * KW1 + (2 * wave + n) * 16 + li] = (acc[m][n][r] + low[m][n][r]) * p.in_scale;
     if constexpr (!DZ16) {
         const int bi = halving_index<RPW>(lane);
         if (bi >= 0) p.bpart[(size_t)blockIdx.x * COUT + wave * RPW + bi] = bs;
@@ -1234,9 +1184,9 @@ hipError_t launch_conv1_u8_wgrad(ConvId id, const ConvIn& in, const float* dz, i
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(UW_WG), lds, st, prm);
         return hipGetLastError();
     };
-    if (id == CONV_S1 && !bf16) return go(conv1_u8_wgrad_kernel<16, 2>, 16, 2);
+    if (id == CONV_S1 && !bf16) return go(conv1_u8_wgrad_kernel<16, 3>, 16, 3);
     if (id != CONV_L1) return hipErrorInvalidValue;
-    return bf16 ? go(conv1_u8_wgrad_kernel<32, 1>, 32, 1) : go(conv1_u8_wgrad_kernel<32, 2>, 32, 2);
+    return bf16 ? go(conv1_u8_wgrad_kernel<32, 1>, 32, 1) : go(conv1_u8_wgrad_kernel<32, 3>, 32, 3);
 }
 
 }  // namespace dqn
