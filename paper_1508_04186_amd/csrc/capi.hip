@@ -146,7 +146,16 @@ struct TdLayout {
 // tiles), which the finalize adds.
 bool fc1w_split(const NetInfo& ni, int B) { return !ni.bf16 && B >= kGemmX6SliceMinRows && ni.H >= 512; }
 
-constexpr int kShareMinBatch = 101;
+// Batches of the large network whose fc1 partial sums (last read by the head)
+// share their room with the weight-gradient partial sums (first written after
+// it).  The room is then in the last-level cache: us of a held-target step,
+// apart and shared, batch 512 289 and 287, 700 379 and 376, 1,024 490 and 487,
+// bf16-input variant 191.1 and 188.9 at 512, 274.5 and 271.0 at 1,024.  Below
+// the two are even (400 262.9 and 262.9, 256 184.6 and 184.7, 128 132.8 and
+// 131.7, bf16 64 89.4 and 90.5); at 2,048, where a step's memory is several
+// times that cache, shared room makes the writes wait for the lines just read
+// (871 and 881, bf16 416 either way).
+constexpr int kShareMinBatch = 512, kShareMaxBatch = 1024;
 
 TdLayout td_layout(const NetInfo& ni, int B, void* ws) {
     TdLayout t{};
@@ -162,15 +171,10 @@ TdLayout td_layout(const NetInfo& ni, int B, void* ws) {
     t.r = cv.take<float>(ws, B);
     t.t = cv.take<uint8_t>(ws, B);
     for (int l = 0; l < ni.n_conv; ++l) t.dconv[l] = cv.take<float>(ws, (int64_t)B * act_elems(ni.d[l]));
-    // From kShareMinBatch samples of the large network the fc1 partial sums
-    // (last read by the head) share their room with the weight-gradient partial
-    // sums (first written after it): the room stays in the last-level cache
-    // (batch 512, 268 -> 261 us a step).  Below, lines freshly read there made
-    // the writes slower (batch 32 102 -> 103 us; small network 41 -> 42).
     const size_t shared = cv.off;
     t.fc1p = cv.take<float>(ws, (int64_t)t.ks * n2 * ni.H);
     const size_t fc1p_end = cv.off;
-    if (ni.n_conv == 3 && B >= kShareMinBatch) cv.off = shared;
+    if (ni.n_conv == 3 && B >= kShareMinBatch && B <= kShareMaxBatch) cv.off = shared;
     for (int l = 0; l < ni.n_conv; ++l) {
         const ConvDims& c = ni.d[l];
         t.chunks[l] = !walk_net(ni) ? conv_wgrad_chunks(ni.conv[l], B)

@@ -20,11 +20,17 @@ F32 = np.float32
 # 127 | 128: the fc1 gradients on bf16 MFMA (small network 255 | 256); 128 |
 # 129: the eight-lane finalize; small network, 80 | 81: the fused and the
 # sample-walking conv kernels; 85 | 86 and 128 | 129: a sample or a run of them
-# per workgroup of the two backward passes (301: runs with a remainder).
+# per workgroup of the two backward passes (301: runs with a remainder); 511 |
+# 512 and 1,024 | 1,025: the fc1 partial sums' room shared with the weight
+# gradients'; 512 | 513: the fc1 gradients in one launch or two, and the
+# forward's wide tiles (with a held target from 1,024); 1,023 | 1,024: the fc1
+# weight gradient in two slices (1,101: the second with a remainder).
 @pytest.mark.parametrize("name,B,target", [
     ("large", 1, "held"), ("large", 24, "held"), ("large", 31, "held"), ("large", 32, "held"), ("large", 33, "same"),
     ("large", 63, "held"), ("large", 85, "held"), ("large", 86, "same"), ("large", 127, "same"), ("large", 128, "same"),
-    ("large", 129, "held"), ("large", 301, "held"), ("small", 63, "held"), ("small", 64, "same"),
+    ("large", 129, "held"), ("large", 301, "held"), ("large", 511, "held"), ("large", 512, "same"),
+    ("large", 513, "held"), ("large", 1023, "held"), ("large", 1024, "same"), ("large", 1025, "held"),
+    ("large", 1101, "same"), ("large", 1101, "held"), ("small", 63, "held"), ("small", 64, "same"),
     ("small", 80, "same"), ("small", 81, "held"), ("small", 127, "held"),
     ("small", 128, "same"), ("small", 129, "held"), ("small", 255, "same"), ("small", 256, "held")])
 def test_td_gradient_at_route_edges(dev, name, B, target):
@@ -41,8 +47,9 @@ def test_td_gradient_at_route_edges(dev, name, B, target):
     assert_grad_close(shape, g, ref["grad"])
 
 
-# 99 | 100 and 256 | 257: conv3's samples per weight-gradient slot.
-@pytest.mark.parametrize("B", [1, 99, 100, 257])
+# 99 | 100 and 256 | 257: conv3's samples per weight-gradient slot; 511 | 512
+# and 1,024 | 1,025: the shared room.
+@pytest.mark.parametrize("B", [1, 99, 100, 257, 511, 512, 1025])
 def test_bf16_td_gradient_at_route_edges(dev, B):
     net, shape = dq.NET_LARGE_BF16, di.NET_L
     th = di.xavier_theta(shape, 260 + B, bias_scale=0.02)
@@ -62,7 +69,8 @@ def test_bf16_td_gradient_at_route_edges(dev, B):
     assert max(errs.values()) <= BF16_TOL, errs
 
 
-@pytest.mark.parametrize("net,B", [(dq.NET_SMALL, 149), (dq.NET_SMALL, 150), (dq.NET_LARGE, 1), (dq.NET_LARGE, 63), (dq.NET_LARGE, 64),
+@pytest.mark.parametrize("net,B", [(dq.NET_SMALL, 149), (dq.NET_SMALL, 150), (dq.NET_LARGE, 1), (dq.NET_LARGE, 63),
+                                   (dq.NET_LARGE, 64), (dq.NET_LARGE, 1023), (dq.NET_LARGE, 1024),
                                    (dq.NET_LARGE, 65), (dq.NET_LARGE_BF16, 1), (dq.NET_LARGE_BF16, 67)])
 def test_forward_at_route_edges(dev, net, B):
     import torch
@@ -77,9 +85,8 @@ def test_forward_at_route_edges(dev, net, B):
     assert_close(host(q), oracle.forward_q(shape, th, s, bf16=bf16), BF16_TOL if bf16 else FP32_TOL, "q")
 
 
-# The float32 kernels scale each sample and each channel's weights by powers
-# of two before their float16 split: uniform rescalings of a layer that cancel
-# in the next leave Q and the other layers' gradients as they were.
+# Uniform rescalings of a layer by a power of two that cancel in the next
+# leave Q and the other layers' gradients as they were.
 @pytest.mark.parametrize("name,B", [("large", 5), ("large", 70), ("small", 90)])
 @pytest.mark.parametrize("exp", [-60, 40])
 def test_td_gradient_under_layer_rescaling(dev, name, B, exp):
