@@ -219,8 +219,8 @@ int dqn_td_gradient(const dqn_net* net, const float* theta, const float* theta_t
  * GPU until the process ends; the call allocates and frees nothing.
  * The batch is limited by that size: when dqn_workspace_bytes(net, batch,
  * DQN_OP_TD_GRADIENT) exceeds 64 MiB the call returns DQN_EWORKSPACE and
- * enqueues nothing.  Every batch up to 289 samples fits for the small
- * network, up to 100 for the large one and up to 93 for its bf16-input
+ * enqueues nothing.  Every batch up to 461 samples fits for the small
+ * network, up to 123 for the large one and up to 116 for its bf16-input
  * variant.  The array needs no clearing between calls (every call writes
  * what it reads).  Every call on one GPU shares that GPU's array: calls that
  * overlap on one GPU (concurrent streams or host threads) race, so serialize

@@ -210,18 +210,6 @@ TdLayout td_layout(const NetInfo& ni, int B, void* ws) {
     return t;
 }
 
-// Largest batch that dqn_td_gradient_noalloc takes (dqn.h).
-int noalloc_limit(const NetInfo& ni) { return ni.n_conv == 2 ? 289 : ni.bf16 ? 93 : 100; }
-
-// Workspace bytes that the TD step asks its caller for: the layout's, and
-// beyond noalloc_limit more than the static scratch, so that the two agree
-// on every batch however small the layout is.
-size_t td_bytes(const NetInfo& ni, int B) {
-    const int lim = noalloc_limit(ni);
-    const size_t least = 2 * kNoAllocScratchBytes / (2 * lim + 1) * std::min(B, lim + 1);
-    return std::max(td_layout(ni, B, nullptr).bytes, (least + 255) / 256 * 256);
-}
-
 struct FwdLayout {
     float* act[3];
     float* fc1p;
@@ -335,8 +323,8 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
         return DQN_EINVAL;
     if (!aligned(ws, 256) || !aligned(theta, 16) || !aligned(tt, 16) || !aligned(grad_out, 16))
         return DQN_EINVAL;
-    if (ws_bytes < td_bytes(ni, batch)) return DQN_EWORKSPACE;
     const TdLayout t = td_layout(ni, batch, ws);
+    if (ws_bytes < t.bytes) return DQN_EWORKSPACE;
     const int B = batch, L = ni.n_conv;
     const float* th = theta;
     const int64_t rec = (int64_t)net->in_c * net->in_h * net->in_w;
@@ -700,7 +688,7 @@ int64_t dqn_workspace_bytes(const dqn_net* net, int32_t batch, int32_t op) {
     if (rc != DQN_OK) return rc;
     if (batch <= 0) return DQN_EINVAL;
     if (op == DQN_OP_FORWARD) return (int64_t)fwd_layout(ni, batch, nullptr).bytes;
-    if (op == DQN_OP_TD_GRADIENT) return (int64_t)td_bytes(ni, batch);
+    if (op == DQN_OP_TD_GRADIENT) return (int64_t)td_layout(ni, batch, nullptr).bytes;
     return DQN_EINVAL;
 }
 
@@ -862,11 +850,10 @@ int dqn_td_gradient_noalloc(const dqn_net* net, const float* theta, const float*
     if (!s || !s_next || !action || !reward || !terminal) return DQN_EINVAL;
     if (!aligned(s, 16) || !aligned(s_next, 16)) return DQN_EINVAL;
     if (batch <= 0) return DQN_EINVAL;
-    // Reject a batch whose workspace exceeds the scratch before touching it.
-    // (The bf16-input variant's 97 is taken too: its layout fits, and it was
-    // taken when 94 to 96 did not fit.)
-    const bool bf16_97 = ni.bf16 && batch == 97;
-    if ((bf16_97 ? td_layout(ni, batch, nullptr).bytes : td_bytes(ni, batch)) > kNoAllocScratchBytes)
+    // Reject a batch whose workspace exceeds the scratch before touching it
+    // (and, before its layout is formed, one whose first layer's outputs do).
+    if (batch > (int64_t)kNoAllocScratchBytes / (8 * act_elems(ni.d[0])) ||
+        td_layout(ni, batch, nullptr).bytes > kNoAllocScratchBytes)
         return DQN_EWORKSPACE;
     const hipStream_t st = (hipStream_t)stream;
     void* ws = nullptr;
@@ -874,7 +861,7 @@ int dqn_td_gradient_noalloc(const dqn_net* net, const float* theta, const float*
     if (rc != DQN_OK) return rc;
     TdSource src{s, s_next, action, reward, terminal, nullptr, nullptr};
     return td_gradient_impl(net, ni, theta, theta_target, src, batch, gamma, grad_out, loss_out,
-                            q_out, y_out, ws, bf16_97 ? td_bytes(ni, batch) : kNoAllocScratchBytes, st);
+                            q_out, y_out, ws, kNoAllocScratchBytes, st);
 }
 
 int dqn_td_gradient_replay(const dqn_net* net, const float* theta, const float* theta_target,

@@ -398,7 +398,7 @@ def test_forward_replay_argument_errors():
                                 FAKE + 2**34, ws, None) == dq.DQN_EINVAL
 
 
-@pytest.mark.parametrize("net,limit", [(dq.NET_SMALL, 289), (dq.NET_LARGE, 100), (dq.NET_LARGE_BF16, 93)])
+@pytest.mark.parametrize("net,limit", [(dq.NET_SMALL, 461), (dq.NET_LARGE, 123), (dq.NET_LARGE_BF16, 116)])
 def test_noalloc_batch_limits_match_the_header(net, limit):
     """dqn_td_gradient_noalloc runs in a 64 MiB static workspace: every batch
     up to the limit that include/dqn.h states fits it, the next does not."""
@@ -406,3 +406,22 @@ def test_noalloc_batch_limits_match_the_header(net, limit):
     sizes = [dq.dqn_workspace_bytes(net, b, dq.DQN_OP_TD_GRADIENT) for b in range(1, limit + 2)]
     assert all(0 < s <= cap for s in sizes[:limit])
     assert sizes[limit] > cap
+
+
+@fake_ptr_test
+@pytest.mark.parametrize("net", [dq.NET_SMALL, dq.NET_LARGE, dq.NET_LARGE_BF16], ids=["small", "large", "large_bf16"])
+def test_noalloc_refuses_exactly_what_exceeds_its_scratch(net):
+    """DQN_EWORKSPACE if and only if dqn_workspace_bytes is above 64 MiB, over
+    every batch about the limits (without a GPU the others end at the lookup
+    of the scratch's address).  A batch whose layout's sizes would overflow is
+    refused too."""
+    L = dq.lib()
+    n = _cnet(net)
+
+    def refused(batch):
+        p = [FAKE + k * 2**32 for k in range(11)]
+        return L.dqn_td_gradient_noalloc(n, *p[:7], batch, ctypes.c_float(0.99), *p[7:], None) == dq.DQN_EWORKSPACE
+
+    for b in range(1, 700):
+        assert refused(b) == (dq.dqn_workspace_bytes(net, b, dq.DQN_OP_TD_GRADIENT) > 64 * 2**20), b
+    assert all(refused(b) for b in (2048, 2**30, 2**31 - 1))

@@ -74,3 +74,27 @@ def test_noalloc_rejects_a_batch_beyond_the_scratch(dev):
     assert e.value.status == dq.DQN_EWORKSPACE
     torch.cuda.synchronize()
     assert torch.isnan(g).all() and torch.isnan(loss).all()   # nothing was enqueued
+
+
+@pytest.mark.parametrize("name,B", [("small", 461), ("large", 123), ("large_bf16", 94), ("large_bf16", 116)])
+def test_noalloc_largest_batches(dev, name, B):
+    """The largest batches that the header states: the same bits as with a
+    workspace of dqn_workspace_bytes, and a canary behind that workspace stays."""
+    import torch
+    net, shape = {"small": (dq.NET_SMALL, di.NET_S), "large": (dq.NET_LARGE, di.NET_L),
+                  "large_bf16": (dq.NET_LARGE_BF16, di.NET_L)}[name]
+    say(f"[noalloc] net={name} batch={B}")
+    th = di.xavier_theta(shape, 900 + B, bias_scale=0.05)
+    s, sn = di.random_states(B, 901 + B), di.random_states(B, 902 + B)
+    a, r, t = di.random_transitions(B, shape.n_actions, 903 + B, p_terminal=0.2)
+    d = [dev_tensor(x) for x in (th, th, s, sn, a.astype(np.int32), r.astype(F32), t.astype(np.uint8))]
+    g0, l0, q0, y0 = _outputs(dev, net, B)
+    g1, l1, q1, y1 = _outputs(dev, net, B)
+    need = dq.dqn_workspace_bytes(net, B, dq.DQN_OP_TD_GRADIENT)
+    room = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=dev)
+    dq.dqn_td_gradient_noalloc(net, *d, 0.99, g0, l0, q0, y0)
+    dq.dqn_td_gradient(net, *d, 0.99, g1, l1, q1, y1, room[:need])
+    torch.cuda.synchronize()
+    assert (room[need:] == 0x5A).all()
+    for x, y_, what in ((g0, g1, "grad"), (l0, l1, "loss"), (q0, q1, "q"), (y0, y1, "y")):
+        assert torch.equal(x, y_), f"{what} differs from dqn_td_gradient"
