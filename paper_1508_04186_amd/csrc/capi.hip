@@ -347,17 +347,16 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
         s0 = ConvIn{src.s, nullptr, rec, 0};
         sn0 = ConvIn{src.s_next, nullptr, rec, 0};
     }
-    // The bf16-input variant reads the network input with the byte-input
-    // conv1 kernels, which need 16-byte aligned samples.
-    if (ni.bf16 && (!conv_s12_fwd_aligned(s0) || !conv_s12_fwd_aligned(sn0))) return DQN_EINVAL;
+    // Every byte-input kernel reads 16-byte units (the entry points check
+    // their pointers and strides).
+    if (!conv_s12_fwd_aligned(s0) || !conv_s12_fwd_aligned(sn0)) return DQN_EINVAL;
     // The bf16-input variant stores the conv layers' outputs as bfloat16
     // values: every reader rounds them to bfloat16 anyway (the next layer's
     // forward and weight gradient, the fc1 contractions) or takes only their
     // sign (the ReLU masks of the input gradients).
     const bool a16 = ni.bf16;
     const bool fusion = g_fusion.load(std::memory_order_relaxed);
-    const bool aligned_in = conv_s12_fwd_aligned(s0) && conv_s12_fwd_aligned(sn0);
-    const bool walk = walk_net(ni) || (walk_td(ni, B) && fusion && aligned_in);
+    const bool walk = walk_net(ni) || (walk_td(ni, B) && fusion);
 
     // The large network's conv2 and conv3 kernels that hold their weights in
     // registers load them from copies in per-lane order, written beside the
@@ -400,13 +399,13 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
     // Forward of s under theta (samples 0..B-1) and of s' under theta^-
     // (samples B..2B-1): one launch per layer, or both conv layers of the
     // small network in one launch at small batch.
-    const bool fused_fwd = !walk && fusion && L == 2 && aligned_in;
-    if (fused_fwd)
+    const bool fused = !walk && fusion;   // (small network)
+    if (fused)
         RUN(DQN_K_CONV12_FWD,
             launch_conv_s12_fwd(s0, sn0, B, 2 * B, th + ni.w_off[0], th + ni.b_off[0], th + ni.w_off[1],
                                 th + ni.b_off[1], tt + ni.w_off[0], tt + ni.b_off[0], tt + ni.w_off[1],
                                 tt + ni.b_off[1], t.act[0], t.act[1], src.replay ? &side : nullptr, st));
-    for (int l = 0; l < L && !fused_fwd; ++l) {
+    for (int l = 0; l < L && !fused; ++l) {
         const int64_t ae = l > 0 ? act_elems(ni.d[l - 1]) : 0;
         if (walk && l == 0) {
             RUN(DQN_K_CONV1_FWD,
@@ -495,20 +494,19 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
     // The small network's conv layers in one launch: conv2's weight gradient,
     // and conv2's input gradient with conv1's weight gradient per (sample,
     // band of conv1 rows).
-    const bool fused_bwd = !walk && fusion && L == 2 && conv_s12_fwd_aligned(s0);
     int chunks_used[3] = {t.chunks[0], t.chunks[1], t.chunks[2]};
     int& chunks0 = chunks_used[0];
     if (walk && L == 2) {
         chunks_used[0] = conv1_u8_wgrad_slots(B);
         chunks_used[1] = conv_wgrad_reg_slots(ni.conv[1], B, false);
     }
-    if (fused_bwd) {
+    if (fused) {
         RUN(DQN_K_CONV12_BWD,
             launch_conv_s12_bwd(s0, t.act[0], t.dconv[1], th + ni.w_off[1], B, t.wpart[1], t.bpart[1],
                                 t.wpart[0], t.bpart[0], st));
         chunks0 = conv_s12_bwd_slots(B);
     }
-    for (int l = L - 1; l >= 0 && !fused_bwd; --l) {
+    for (int l = L - 1; l >= 0 && !fused; --l) {
         const ConvIn in = l == 0 ? s0 : ConvIn{t.act[l - 1], nullptr, act_elems(ni.d[l - 1]) * 4, 0};
         const float scale = l == 0 ? (float)(1.0 / 255.0) : 1.f;
         if (!walk) {
@@ -737,10 +735,11 @@ int forward_impl(const dqn_net* net, const NetInfo& ni, const float* theta, cons
     if (ws_bytes < f.bytes) return DQN_EWORKSPACE;
     f = fwd_layout(ni, batch, ws);
     const float* th = theta;
-    const bool fusable = g_fusion.load(std::memory_order_relaxed) && ni.n_conv == 2 && conv_s12_fwd_aligned(in0);
-    const bool walk = walk_net(ni) || (walk_fwd(ni, batch) && fusable);
-    const bool fused_fwd = fusable && !walk;
-    if (fused_fwd)
+    if (!conv_s12_fwd_aligned(in0)) return DQN_EINVAL;
+    const bool fusion = g_fusion.load(std::memory_order_relaxed);
+    const bool walk = walk_net(ni) || (walk_fwd(ni, batch) && fusion);
+    const bool fused = !walk && fusion;   // (small network)
+    if (fused)
         RUN(DQN_K_CONV12_FWD,
             launch_conv_s12_fwd(in0, in0, batch, batch, th + ni.w_off[0], th + ni.b_off[0],
                                 th + ni.w_off[1], th + ni.b_off[1], th + ni.w_off[0], th + ni.b_off[0],
@@ -754,7 +753,7 @@ int forward_impl(const dqn_net* net, const NetInfo& ni, const float* theta, cons
             r.p3a = f.fpk[1];
         }
     }
-    for (int l = 0; l < ni.n_conv && !fused_fwd; ++l) {
+    for (int l = 0; l < ni.n_conv && !fused; ++l) {
         if (walk && l == 0) {
             RUN(DQN_K_CONV1_FWD,
                 launch_conv1_u8_fwd(ni.conv[0], in0, in0, batch, batch, th + ni.w_off[0], th + ni.b_off[0], th + ni.w_off[0],

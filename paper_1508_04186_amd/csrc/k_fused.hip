@@ -601,8 +601,6 @@ __global__ __launch_bounds__(WG) void conv_s12_bwd_kernel(WgradParams w, S1BwdPa
 
 }  // namespace
 
-bool conv_s12_fwd_supported(ConvId c1, ConvId c2) { return c1 == CONV_S1 && c2 == CONV_S2; }
-
 bool conv_s12_fwd_aligned(const ConvIn& in) {
     return ((uintptr_t)in.base & 15) == 0 && (in.stride & 15) == 0;
 }
