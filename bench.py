@@ -399,13 +399,13 @@ def measured_traffic(config, name):
     return None
 
 
-# Large-network float32 kernels that run their contraction on f16 MFMA with
-# scaled two-term float16 splits of float32 operands: the number of f16
-# products per float32 product (both operands split: 3 of the 4 pairs; one
-# operand exact in float16, the input bytes: 2).  Their matrix ceiling is the
-# dense peak (f16 and bf16 alike) divided by that count.
-SPLIT_PRODUCTS = {"conv1_fwd": 2, "conv1_wgrad": 2, "conv2_fwd": 3, "conv3_fwd": 3, "conv2_bwd": 3, "conv3_bwd": 3,
-                  "fc1_fwd": 3, "fc1_bwd": 3, "fc1_wgrad": 3, "fc1_dgrad": 3}
+# Large-network float32 kernels that run their contraction on bf16 MFMA with
+# exact three-term bf16 splits of float32 operands: the number of bf16
+# products per float32 product (both operands split: 6 of the 9 pairs; one
+# operand exact in bf16, the input bytes: 3).  Their matrix ceiling is the
+# bf16 dense peak divided by that count.
+SPLIT_PRODUCTS = {"conv1_fwd": 3, "conv1_wgrad": 3, "conv2_fwd": 6, "conv3_fwd": 6, "conv2_bwd": 6, "conv3_bwd": 6,
+                  "fc1_fwd": 6, "fc1_bwd": 6, "fc1_wgrad": 6, "fc1_dgrad": 6}
 
 
 def roofline(work, name, avg_us, launches, per_step_launches, raw_us=None, config=None,
@@ -426,8 +426,8 @@ def roofline(work, name, avg_us, launches, per_step_launches, raw_us=None, confi
         out["per_launch"]["event_pair_us"] = round(raw_us, 3)
         out["per_launch"]["event_overhead_us"] = round(raw_us - avg_us, 3)
     if products > 1:
-        out["peak_basis"] = (f"float32 contraction on f16 MFMA, {products} f16 products per float32 product "
-                             f"(scaled two-term splits): f16 dense {PEAK_BF16_MFMA / 1e12:.0f} TFLOP/s / {products}")
+        out["peak_basis"] = (f"float32 contraction on bf16 MFMA, {products} bf16 products per float32 product "
+                             f"(exact three-term splits): bf16 dense {PEAK_BF16_MFMA / 1e12:.0f} TFLOP/s / {products}")
         out["frac_of_fp32_matrix_peak"] = round(achieved / (PEAK_FP32_MFMA / 1e12), 6)
     return out
 

@@ -133,8 +133,8 @@ def test_apply_matches_oracle(dev, rule, n):
 # ---------------------------------------------------------------------------
 # dqn_forward
 
-# large 200: the fp32 implicit-GEMM forward of conv2/conv3 (128 to 255 rows);
-# small 1030: the one-wave-per-state head (from 1,024 states)
+# large 70, 200: conv2 and conv3 walking whole samples (3: a workgroup per
+# output tile); small 1030: the one-wave-per-state head (from 1,024 states)
 @pytest.mark.parametrize("name,batch", [("small", 1), ("small", 45), ("large", 3), ("large", 70), ("large", 200),
                                         ("small", 1030)])
 def test_forward_q_and_greedy_actions(dev, name, batch):
@@ -264,11 +264,10 @@ def _run_td(dev, net, th, tt, s, sn, a, r, t, gamma):
     return host(g), float(host(loss)[0]), host(q), host(y)
 
 
-# The large network's fp32 kernel choice depends on the batch: below 64
-# samples per conv launch the per-layer kernels; 64 runs the paired backward
-# with the implicit-GEMM forward (128 rows for s and s'); 100 the unpaired
-# per-layer weight and input gradients and the fc1 GEMMs with the same
-# forward; 128 and above (the large-batch tests) the register-weight kernels.
+# The large network's fp32 kernel choice depends on the batch: to 32 samples a
+# workgroup per conv output tile in the forward, 64 and 100 walk whole samples,
+# the fc1 forward on the bf16 split and its gradients on fp32 MFMA (from 128,
+# the large-batch tests, on the split too).
 # From 64 samples the large network's states are drawn with unique
 # gradients (about 21,000 ReLUs per sample: uniform random bytes put some
 # pre-activation within float32 rounding of zero in most batches that size).

@@ -36,8 +36,9 @@ def _run_td(dev, net, th, tt, s, sn, a, r, t, gamma):
     return host(g), float(host(loss)[0]), host(q), host(y)
 
 
-# large 517: ragged weight-gradient slots (the float32 six-product kernels:
-# conv2 slots of 5 samples, the last of 2; conv3 slots of 3, the last of 1)
+# large 517: ragged runs of samples (conv2's and conv3's input gradients: 5, the
+# last of 2; weight-gradient slots: conv2 7, the last of 6, conv3 5, the last of
+# 2, conv1 3, the last of 1)
 @pytest.mark.parametrize("name,B,target", [("small", 700, "same"), ("small", 1024, "held"),
                                            ("large", 131, "held"), ("large", 256, "held"),
                                            ("large", 517, "held"), ("large", 2048, "same")])
