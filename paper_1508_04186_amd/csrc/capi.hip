@@ -88,25 +88,23 @@ int identify(const dqn_net* net, NetInfo* ni) {
 
 inline int64_t act_elems(const ConvDims& c) { return (int64_t)c.cout * c.oh * c.ow; }
 
-// Largest batch whose two fc1 gradients share one launch in float32 (step of
-// the large network, one launch against two: batch 100 128.2 against 131.7
-// us, 256 175.3 against 176.1, 512 261.7 against 263.8; small network, 512
-// 213 against 222).
-constexpr int kFc1PairMaxBatch = 512;
 // dqn_profile_set_fusion (a measurement switch; read once per call)
 std::atomic<bool> g_fusion{true};
 // The large network runs on the kernels that walk whole samples (byte-input
 // conv1, register-weight conv2/conv3) at every batch, in both precisions: us
 // per float32 step with a held target against the per-layer kernels it had
-// below 128 samples, batch 16 104 against 113, 32 107 against 134, 64 120
-// against 183, 100 132 against 260.
+// below 128 samples, batch 16 82 against 111, 32 87 against 133, 64 98 against
+// 182, 100 115 against 262.
 inline bool walk_net(const NetInfo& ni) { return ni.n_conv == 3; }
 // The small network does so from this batch (TD step) or this many states
-// (forward); below, its fused two-layer launches are fewer (us, fused against
-// walking: step of 64 52.4 and 58.5, 80 59.8 and 60.6, 100 72.1 and 64.1, 512
-// 216 and 118, 2,048 815 and 321; forward of 128 states 27.7 and 28.8, 200
-// 36.8 and 32.8, 8,192 626 and 283).
-constexpr int kSmallWalkBatch = 81, kSmallWalkStates = 150;
+// (forward); below, its fused two-layer launches are fewer.  A forward (us,
+// fused against walking): 80 states 17.8 and 21.0, 100 22.0 and 20.9, 128 24.8
+// and 23.6, 200 32.7 and 26.2, 8,192 636 and 280.  A step alone on the GPU: 64
+// 50.5 and 48.9, 80 58.4 and 52.6, 100 69.9 and 55.5; but the walking kernels
+// take a compute unit's whole LDS, so steps on several streams share the chip
+// less well (us an update, eight replicas of 64 47.8 and 55.5, of 81 49.5 and
+// 54.5, of 100 54.5 either way; four of 112 62.6 and 55.1).
+constexpr int kSmallWalkBatch = 81, kSmallWalkStates = 100;
 inline bool walk_td(const NetInfo& ni, int B) { return walk_net(ni) || B >= kSmallWalkBatch; }
 inline bool walk_fwd(const NetInfo& ni, int n) { return walk_net(ni) || n >= kSmallWalkStates; }
 
@@ -467,9 +465,13 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
     RUN(DQN_K_HEAD, launch_head_td(ni.H, ni.A, h, st));
 
     // fc1: weight gradient and the masked gradient of the last conv output;
-    // then the conv layers, last to first.  At small batch each layer's two
-    // independent backward kernels share one launch.
-    if (!ni.bf16 && B <= kFc1PairMaxBatch) {
+    // then the conv layers, last to first.  Each layer's two independent
+    // backward passes share one launch.
+    // (fc1 in float32, unless the weight gradient is split into k-slices, in one
+    // launch: us of a held-target step, two launches against one, batch 400 275
+    // and 264, 600 331 and 325, 1,000 494 and 476; small network, 512 132 and
+    // 125, 2,048 355 and 350.)
+    if (!ni.bf16 && !t.fc1w_part) {
         RUN(DQN_K_FC1_BWD,
             launch_gemm_wgrad_dgrad(ni.H, ni.flat, B, t.dz1, xlast, grad_out + ni.w_off[L],
                                     th + ni.w_off[L], t.dconv[L - 1], st));
@@ -485,7 +487,7 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
         } else {
             RUN(DQN_K_FC1_WGRAD,
                 launch_gemm(GEMM_TN, ni.H, ni.flat, B, dzA, ni.H, xlast, ni.flat, grad_out + ni.w_off[L], ni.flat, 1,
-                            (B + 31) / 32 * 32, 0, nullptr, ni.bf16, st));
+                            (B + 31) / 32 * 32, 0, nullptr, true, st));
         }
         RUN(DQN_K_FC1_DGRAD,
             launch_gemm(GEMM_NN, B, ni.flat, ni.H, dzA, ni.H, th + ni.w_off[L], ni.flat, t.dconv[L - 1], ni.flat, 1,
