@@ -46,7 +46,7 @@ typedef enum {
     DQN_K_CONV3_DGRAD = 12,
     DQN_K_FINALIZE = 13,
     DQN_K_APPLY = 14,
-    DQN_K_FC1_BWD = 15,     /* fc1 weight + input gradient in one launch (float32; the large network below a batch of 1,024) */
+    DQN_K_FC1_BWD = 15,     /* fc1 weight + input gradient in one launch (float32) */
     DQN_K_CONV2_BWD = 16,   /* conv2 weight + input gradient in one launch (float32) */
     DQN_K_CONV3_BWD = 17,   /* conv3 weight + input gradient in one launch (float32) */
     DQN_K_FINALIZE_APPLY = 18, /* finalize with the update applied (dqn_train_steps) */

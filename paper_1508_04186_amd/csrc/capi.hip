@@ -135,14 +135,8 @@ struct TdLayout {
     __bf16* dz1h;         // dz1 in bfloat16 (bf16-input variant), else null
     float *wpk2, *wpk3;   // repacked conv2/conv3 weights of the input gradients (large network)
     float *fpk[2][2];     // ... the forward's: [layer conv2, conv3][set theta, theta^-]
-    float* fc1w_part;     // the float32 fc1 weight gradient's k-slices (large batch, wide layer), else null
     size_t bytes;
 };
-
-// The float32 fc1 weight gradient of a large batch and a 512-wide hidden
-// layer is computed as kGemmX6WgradSlices k-slices of partial sums (larger
-// tiles), which the finalize adds.
-bool fc1w_split(const NetInfo& ni, int B) { return !ni.bf16 && B >= kGemmX6SliceMinRows && ni.H >= 512; }
 
 // Batches of the large network whose fc1 partial sums (last read by the head)
 // share their room with the weight-gradient partial sums (first written after
@@ -203,7 +197,6 @@ TdLayout td_layout(const NetInfo& ni, int B, void* ws) {
         for (int w = 0; w < 2; ++w) t.fpk[0][w] = cv.take<float>(ws, fwd_pack_floats(CONV_S2));
     }
     if (ni.bf16) t.dz1h = cv.take<__bf16>(ws, (int64_t)B * ni.H);
-    if (fc1w_split(ni, B)) t.fc1w_part = cv.take<float>(ws, (int64_t)kGemmX6WgradSlices * ni.H * ni.flat);
     t.bytes = cv.off;
     return t;
 }
@@ -467,31 +460,24 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
     // fc1: weight gradient and the masked gradient of the last conv output;
     // then the conv layers, last to first.  Each layer's two independent
     // backward passes share one launch.
-    // (fc1 in float32, unless the weight gradient is split into k-slices, in one
-    // launch: us of a held-target step, two launches against one, batch 400 275
-    // and 264, 600 331 and 325, 1,000 494 and 476; small network, 512 132 and
-    // 125, 2,048 355 and 350.)
-    if (!ni.bf16 && !t.fc1w_part) {
+    // (fc1 in float32: us of a held-target step, two launches against one,
+    // batch 400 275 and 264, 600 331 and 325, 1,000 494 and 476, and against a
+    // launch of 128x128 tiles over two slices of the batch, 1,100 518 and 501,
+    // 2,048 863 and 848; small network, 512 132 and 125, 2,048 355 and 350.)
+    if (!ni.bf16) {
         RUN(DQN_K_FC1_BWD,
             launch_gemm_wgrad_dgrad(ni.H, ni.flat, B, t.dz1, xlast, grad_out + ni.w_off[L],
                                     th + ni.w_off[L], t.dconv[L - 1], st));
     } else {
         // the bf16-input variant reads the head's bfloat16 copy of dz1 (the
         // same rounding the staging would apply)
-        const float* dzA = t.dz1h ? (const float*)t.dz1h : t.dz1;
-        if (t.fc1w_part) {   // k-slices of ceil(B / 128) * 64 samples (the last one at most that)
-            constexpr int S = kGemmX6WgradSlices;
-            RUN(DQN_K_FC1_WGRAD,
-                launch_gemm(GEMM_TN, ni.H, ni.flat, B, t.dz1, ni.H, xlast, ni.flat, t.fc1w_part, ni.flat, S,
-                            (B + 64 * S - 1) / (64 * S) * 64, (int64_t)ni.H * ni.flat, nullptr, false, st));
-        } else {
-            RUN(DQN_K_FC1_WGRAD,
-                launch_gemm(GEMM_TN, ni.H, ni.flat, B, dzA, ni.H, xlast, ni.flat, grad_out + ni.w_off[L], ni.flat, 1,
-                            (B + 31) / 32 * 32, 0, nullptr, true, st));
-        }
+        const float* dzA = (const float*)t.dz1h;
+        RUN(DQN_K_FC1_WGRAD,
+            launch_gemm(GEMM_TN, ni.H, ni.flat, B, dzA, ni.H, xlast, ni.flat, grad_out + ni.w_off[L], ni.flat, 1,
+                        (B + 31) / 32 * 32, 0, nullptr, true, st));
         RUN(DQN_K_FC1_DGRAD,
             launch_gemm(GEMM_NN, B, ni.flat, ni.H, dzA, ni.H, th + ni.w_off[L], ni.flat, t.dconv[L - 1], ni.flat, 1,
-                        (ni.H + 31) / 32 * 32, 0, xlast, ni.bf16, st));
+                        (ni.H + 31) / 32 * 32, 0, xlast, true, st));
     }
     // The small network's conv layers in one launch: conv2's weight gradient,
     // and conv2's input gradient with conv1's weight gradient per (sample,
@@ -572,8 +558,6 @@ int td_gradient_impl(const dqn_net* net, const NetInfo& ni, const float* theta,
     fa.grad_base = grad_out;
     fa.fc1w_off = ni.w_off[L];
     fa.fc1w_count = (int64_t)ni.H * ni.flat;
-    fa.fc1w_part = t.fc1w_part;
-    fa.fc1w_slices = t.fc1w_part ? kGemmX6WgradSlices : 0;
     fa.spart = t.spart;
     fa.schunks = finalize_sample_chunks(B);
     if (upd)

@@ -22,9 +22,7 @@ F32 = np.float32
 # sample-walking conv kernels; 85 | 86 and 128 | 129: a sample or a run of them
 # per workgroup of the two backward passes (301: runs with a remainder); 511 |
 # 512 and 1,024 | 1,025: the fc1 partial sums' room shared with the weight
-# gradients', and the forward's wide tiles (held: from 1,024); 1,023 | 1,024:
-# the fc1 gradients in one launch, or in two with the weight gradient in two
-# slices (1,101: the second with a remainder).
+# gradients', and the forward's wide tiles (held: from 1,024; 1,101: remainders).
 @pytest.mark.parametrize("name,B,target", [
     ("large", 1, "held"), ("large", 24, "held"), ("large", 31, "held"), ("large", 32, "held"), ("large", 33, "same"),
     ("large", 63, "held"), ("large", 85, "held"), ("large", 86, "same"), ("large", 127, "same"), ("large", 128, "same"),
