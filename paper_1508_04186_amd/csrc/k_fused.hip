@@ -674,8 +674,8 @@ struct U8FwdParams {
 
 // A workgroup per two channels of a copy.  The copies need only the weights,
 // and nothing reads them before the second layer, so they ride along: a
-// launch of their own took 4 us a step (32 states acted on 33.4 -> 30.2 us,
-// step of 32 samples 87.4 -> 83.2, of 256 160 -> 158.7).
+// launch of their own took 4 us a step (with copies of two planes, 32 states
+// acted on 33.4 -> 30.2 us, step of 32 samples 87.4 -> 83.2).
 constexpr int U8F_RBLOCKS = kRepackChannels / 2;
 
 constexpr size_t u8f_lds(int cout, int parts) {
