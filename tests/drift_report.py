@@ -20,8 +20,8 @@ precision; exact zeros, from ReLUs that are off, are not).  Under AdaGrad from a
 about lr * sign(g), so a sign decided by rounding moves that parameter by up
 to 2 lr (the reading of Sec. IV.D.2's AdaGrad that the tests follow).
 
-Part 3: for the large network in float32 at 64 and 256 states (the
-per-layer and the large-batch conv kernels), the GPU's conv outputs and fc1
+Part 3: for the large network in float32 at 64 and 256 states (a workgroup
+per conv output tile, and walking whole samples), the GPU's conv outputs and fc1
 sums are read back from dqn_forward's workspace and compared with float64
 pre-activations z of the same layer computed from the float64 activations
 below (an independent numpy formulation): the normalized error
