@@ -60,11 +60,12 @@ typedef enum {
  *   DQN_FP32  float32 operands and accumulation.  Some contractions run on
  *             16-bit matrix instructions with each float32 operand split into
  *             three bfloat16 terms whose products accumulate in float32.  The
- *             terms hold all 24 bits of the operand (from magnitudes of
- *             2^-110 on) and have its exponent, so the error against float64
- *             is that of float32 sums whatever magnitudes stand side by side,
- *             and a state or sample that overflows spoils no other one's
- *             results (input bytes are exact in one term);
+ *             terms hold all 24 bits of the operand (magnitudes of 2^-110 to
+ *             3.39e38) and have its exponent, so the error against float64 is
+ *             that of float32 sums whatever magnitudes stand side by side.  A
+ *             state that overflows spoils no other state's Q; an infinite
+ *             activation makes that state's own next sums NaN, of which ReLU
+ *             keeps 0 (input bytes are exact in one term);
  *   DQN_BF16  the bf16-input variant, large network only: every operand of
  *             the conv and fc1 contractions (weights, input activations,
  *             back-propagated gradients) is rounded to bfloat16 (round to
