@@ -72,9 +72,10 @@ def _forward(dev, net, th, s):
     return host(q)
 
 
-# Sizes of the fc1 kernels: split forward and gradients (large from 64 states
-# of a step, 128 of a forward; small 128 and 256), 1,024: 128-wide tiles.
-@pytest.mark.parametrize("name,B,layer", [("large", B, layer) for layer in ("fc1", "conv3", "conv2", "conv1") for B in (40, 130, 301)] +
+# Both sides of the sizes at which the fc1 gradients change kernels (large 128,
+# small 256); 301: runs of samples in the conv kernels.
+@pytest.mark.parametrize("name,B,layer", [("large", B, layer) for layer in ("fc1", "conv3", "conv2", "conv1")
+                                          for B in (40, 130, 301)] +
                          [("small", B, layer) for layer in ("fc1", "conv2", "conv1") for B in (90, 257)])
 def test_td_gradient_under_unit_rescaling(dev, name, B, layer):
     net, shape = NETS[name]
@@ -170,8 +171,9 @@ def test_gradient_of_quiet_samples_among_ordinary_ones(dev, name, B):
 
 
 # The conv kernels: large to 64 states (a workgroup per tile) and above (runs
-# of samples, the last short at 301), small from 150.
-@pytest.mark.parametrize("name,layer,B", [("large", layer, B) for layer in ("conv1", "conv2", "conv3") for B in (20, 65, 301)] +
+# of samples, the last short at 301), small from 100.
+@pytest.mark.parametrize("name,layer,B", [("large", layer, B) for layer in ("conv1", "conv2", "conv3")
+                                          for B in (20, 65, 301)] +
                          [("small", layer, B) for layer in ("conv1", "conv2") for B in (150, 600)])
 def test_forward_under_unit_rescaling(dev, name, layer, B):
     net, shape = NETS[name]
